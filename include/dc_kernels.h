@@ -91,6 +91,11 @@ int dc_conv2d_backward_filter(const dc_conv_shape *sh, const float *x, const flo
  * inspection and tuning. */
 int dc_conv2d_plan_info(const dc_conv_shape *sh, int pass, int32_t *out);
 
+/* The form in which that plan multiplies: *split = 1 where each float32 operand
+ * is split into two half-precision terms (three products per pair), 0 for
+ * float32 products (always, on plan sources 3 and 4).  Host only. */
+int dc_conv2d_plan_split(const dc_conv_shape *sh, int pass, int32_t *split);
+
 /* Every plan the pass can be launched with for this shape, as (tile M, tile N,
  * split-K factor) triples: writes min(cap, count) triples to out (3 int32
  * each; out may be NULL when cap is 0) and the number available to *count.

@@ -118,6 +118,7 @@ _SIGS = {
     "dc_timeline": (ctypes.c_int, [c_vp, _P(c_i64), ctypes.c_int]),
     "dc_conv2d_workspace_bytes": (c_sz, [_P(ConvShape)]),
     "dc_conv2d_plan_info": (ctypes.c_int, [_P(ConvShape), ctypes.c_int, _P(c_i32)]),
+    "dc_conv2d_plan_split": (ctypes.c_int, [_P(ConvShape), ctypes.c_int, _P(c_i32)]),
     "dc_conv2d_plan_candidates": (ctypes.c_int, [_P(ConvShape), ctypes.c_int, _P(c_i32), ctypes.c_int, _P(c_i32)]),
     "dc_conv2d_set_plan": (ctypes.c_int, [_P(ConvShape), ctypes.c_int, ctypes.c_int, ctypes.c_int, ctypes.c_int]),
     "dc_conv2d_forward": (ctypes.c_int, [_P(ConvShape), c_vp, c_vp, c_vp, ctypes.c_int, c_vp, c_vp, c_sz, c_vp]),
@@ -289,6 +290,14 @@ def conv_plan_info(shape, pas):
     sh = ConvShape(*shape)
     call("dc_conv2d_plan_info", ctypes.byref(sh), pas, out)
     return tuple(out)
+
+
+def conv_plan_split(shape, pas):
+    """Whether one conv pass multiplies operands split into two half-precision terms."""
+    sh = ConvShape(*shape)
+    out = c_i32()
+    call("dc_conv2d_plan_split", ctypes.byref(sh), pas, ctypes.byref(out))
+    return bool(out.value)
 
 
 def conv_plan_candidates(shape, pas):

@@ -158,6 +158,17 @@ extern "C" int dc_conv2d_plan_info(const dc_conv_shape *sh, int pass, int32_t *o
     return DC_OK;
 }
 
+extern "C" int dc_conv2d_plan_split(const dc_conv_shape *sh, int pass, int32_t *split) {
+    clear_error();
+    ConvGeom g;
+    DC_TRY(conv_setup(sh, &g));
+    if (pass < 0 || pass > 2 || !split)
+        return fail(DC_EINVAL, "pass must be 0, 1 or 2 and split non-NULL");
+    const GemmPlan pl = plan_gemm(g, pass);
+    *split = pl.split && !pl.fc && !pl.direct;
+    return DC_OK;
+}
+
 extern "C" int dc_conv2d_plan_candidates(const dc_conv_shape *sh, int pass, int32_t *out, int cap, int32_t *count) {
     clear_error();
     ConvGeom g;

@@ -127,3 +127,19 @@ def test_rgb_layer_takes_the_direct_kernels(shape, direct):
         finally:
             D.conv_set_plan(shape, 0, 0)
         assert D.conv_plan_info(shape, 0)[7] == 4
+
+
+def test_plan_split_names_the_form():
+    """Operands are split from 5e8 flops and a reduction of 96 on, where they are read as float4s; the kernels
+    of plan sources 3 and 4 never split."""
+    big = (8, 28, 28, 96, 128, 3, 3, 1, 1, 1)            # 1.4e9 flops
+    assert [D.conv_plan_split(big, p) for p in range(3)] == [True, True, True]
+    assert [D.conv_plan_split((2,) + big[1:], p) for p in range(3)] == [False] * 3   # 3.5e8 flops
+    short = (64, 28, 28, 64, 256, 1, 1, 1, 0, 0)         # forward reduction of 64
+    assert [D.conv_plan_split(short, p) for p in range(3)] == [False, True, True]
+    odd = (8, 28, 28, 96, 126, 3, 3, 1, 1, 1)            # 126 filters: dy is not read as float4s
+    assert [D.conv_plan_split(odd, p) for p in range(3)] == [True, False, False]
+    assert not D.conv_plan_split((32, 1, 1, 25088, 4096, 1, 1, 1, 0, 0), 1)
+    assert not D.conv_plan_split((32, 224, 224, 3, 64, 3, 3, 1, 1, 1), 0)
+    with pytest.raises(D.DcError):
+        D.conv_plan_split(big, 3)
