@@ -34,9 +34,14 @@ size_t dc_conv2d_workspace_bytes(const dc_conv_shape *sh);
 
 /* y[n,p,q,k] = bias[k] + sum over r, s, c of x[n, p*stride+r-pad, q*stride+s-pad_w, c] * w[k,r,s,c],
  * then max(., 0) if relu; implicit GEMM on the matrix cores, float32 sums.  bias
- * may be NULL.  Large passes multiply operands split into two half-precision
- * terms: together 23 to 24 bits, fewer for values more than 2^26 below the
- * largest of their tile. */
+ * may be NULL.  Large passes (dc_conv2d_plan_split) multiply operands split into
+ * two half-precision terms, which hold a value to 2^-23 of itself or to 2^-24 of
+ * the largest magnitude in its own row (here an output pixel's window, or a
+ * filter), whichever is coarser.  What other rows hold has no part in it: where
+ * rows of one tile lie further apart than the terms reach, and where a sum is
+ * not finite, the tile is evaluated again by float32 products (a pass of such
+ * tiles alone takes three times as long).  The same holds for the two backward
+ * passes, whose rows are the values of dy, w or x that meet in one result. */
 int dc_conv2d_forward(const dc_conv_shape *sh, const float *x, const float *w, const float *bias,
                       int relu, float *y, void *ws, size_t ws_bytes, void *stream);
 

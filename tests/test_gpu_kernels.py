@@ -735,6 +735,65 @@ def test_conv_split_operands(shape, spread):
     assert rel_err(dw, dw_ref) <= tol(n * P * Q)
 
 
+APART_SHAPES = [s for s in SPLIT_SHAPES if s[7] == 1] + [(10, 30, 30, 96, 144, 3, 3, 2, 1, 1),
+                                                         (16, 28, 28, 128, 160, 1, 1, 1, 0, 0)]
+
+
+@pytest.mark.parametrize("shape", APART_SHAPES, ids=str)
+@pytest.mark.parametrize("side", ["rows", "columns"])
+def test_conv_split_rows_apart(shape, side):
+    """A row's result does not depend on how large its neighbours are.  Every other row of one operand (an
+    image or pixel of x and dy, a filter or channel of w, a filter of dy, a channel of x) is 2^-gap of the
+    rest, from just within what the tile's common scale holds to far beyond what it can; dividing the result by
+    the same powers of two must give the even operands' result to the float32 bar."""
+    n, h, w, c, k, r, s, st, pad, pad_w = shape
+    P, Q = out_hw(h, r, st, pad), out_hw(w, s, st, pad_w)
+    seed = sum(shape) + 1
+    x, wt = synth.random_tensor(seed, (n, h, w, c)), synth.random_tensor(seed + 1, (k, r, s, c))
+    dy = synth.random_tensor(seed + 2, (n, P, Q, k))
+    refs = [OC.conv2d_forward(x, wt, np.zeros(k, np.float32), st, (pad, pad_w)),
+            OC.conv2d_backward_data(dy, wt, (h, w), st, (pad, pad_w)),
+            OC.conv2d_backward_filter(x, dy, (r, s), st, (pad, pad_w))]
+    assert all(D.conv_plan_split(shape, p) for p in range(3))
+    for gap in (24, 28, 40, 60):
+        def alt(*dims):   # 1, 2^-gap, 1, ...
+            return np.where(np.arange(np.prod(dims)) % 2, 2.0 ** -gap, 1.0).astype(np.float32).reshape(dims)
+        if side == "rows":
+            pix = alt(n, h, w, 1) if r == s == 1 else alt(n, 1, 1, 1)   # a 1 x 1 window is one pixel
+            dyk = dy * alt(1, 1, 1, k)
+            y, dx, _ = _passes(shape, x * pix, wt, dy * pix)
+            dw = _passes(shape, x, wt, dyk)[2]
+            got = [y / pix, dx / pix, dw / alt(k, 1, 1, 1)]
+        else:
+            y = _passes(shape, x, wt * alt(k, 1, 1, 1), dy)[0]
+            dx = _passes(shape, x, wt * alt(1, 1, 1, c), dy)[1]
+            dw = _passes(shape, x * alt(1, 1, 1, c), wt, dy)[2]
+            got = [y / alt(1, 1, 1, k), dx / alt(1, 1, 1, c), dw / alt(1, 1, 1, c)]
+        for name, a, ref, terms in zip(("y", "dx", "dw"), got, refs, (r * s * c, r * s * k, n * P * Q)):
+            assert rel_err(a, ref) <= tol(terms), (name, gap, rel_err(a, ref))
+
+
+def test_conv_split_one_huge_value():
+    """One value of 1e30 in x and in dy: the outputs that it does not reach are what they are without it."""
+    shape = (4, 23, 21, 112, 152, 3, 3, 1, 1, 1)
+    n, h, w, c, k, r, s, st, pad, pad_w = shape
+    assert all(D.conv_plan_split(shape, p) for p in range(3))
+    x, wt = synth.random_tensor(21, (n, h, w, c)), synth.random_tensor(22, (k, r, s, c))
+    dy = synth.random_tensor(23, (n, h, w, k))
+    ref = _passes(shape, x, wt, dy)
+    x[1, 7, 8, 30], dy[2, 9, 10, 77] = 1e30, 1e30
+    y, dx, dw = _passes(shape, x, wt, dy)
+    far = np.ones((n, h, w, 1), dtype=bool)
+    far[1, 6:9, 7:10] = False
+    assert rel_err(y * far, ref[0] * far) <= tol(r * s * c)
+    far[...] = True
+    far[2, 8:11, 9:12] = False
+    assert rel_err(dx * far, ref[1] * far) <= tol(r * s * k)
+    far = np.ones((k, 1, 1, c), dtype=bool)
+    far[77], far[:, :, :, 30] = False, False
+    assert rel_err(dw * far, ref[2] * far) <= tol(n * h * w)
+
+
 def test_conv_split_operands_nonfinite():
     """Infinities and NaNs come out where float32 products put them: an infinite input gives
     infinities (or NaNs where it meets a zero weight) in its own windows only, and a value that
