@@ -216,6 +216,11 @@ PLAN_SHAPES = [
     (3, 15, 15, 32, 48, 3, 3, 2, 1, 1),    # strided: four dgrad phases
     (2, 17, 17, 32, 48, 1, 7, 1, 0, 3),    # 1 x 7 filter, columns padded only
     (2, 20, 20, 3, 16, 3, 3, 1, 1, 1),     # C = 3: channel-padded forward and wgrad
+    # 5e8 flops or more, every pass on split operands: lean stages on ragged tiles; general stages;
+    # four dgrad phases of one to four taps, whose later splits hold no stage
+    (4, 23, 21, 112, 152, 3, 3, 1, 1, 1),
+    (9, 31, 33, 36, 100, 3, 3, 1, 1, 1),
+    (10, 30, 30, 96, 144, 3, 3, 2, 1, 1),
 ]
 
 
@@ -236,6 +241,7 @@ def test_every_plan_matches_oracle(shape):
             OC.conv2d_backward_filter(x, dy, (r, s), st, (pad, pad_w))]
     bars = [tol(r * s * c), tol(r * s * k), tol(n * P * Q)]
     sh = conv_shape(*shape)
+    assert [D.conv_plan_split(shape, p) for p in range(3)] == [2.0 * n * P * Q * k * r * s * c >= 5e8] * 3
     xd, wd_, bd, dyd = dev(x), dev(wt), dev(b), dev(dy)
     tried = 0
     for pas in range(3):
@@ -687,15 +693,16 @@ SPLIT_SHAPES = [
     # stages; general stages (c % 16 != 0); a strided data gradient whose phases differ
     (4, 23, 21, 112, 152, 3, 3, 1, 1, 1),
     (9, 31, 33, 36, 100, 3, 3, 1, 1, 1),
-    (5, 30, 30, 96, 144, 3, 3, 2, 1, 1),
+    (10, 30, 30, 96, 144, 3, 3, 2, 1, 1),
     # images of fewer pixels than a stage (the filter gradient steps whole images)
     (160, 3, 3, 208, 160, 3, 3, 1, 1, 1),
 ]
 
 
 def _passes(shape, x, wt, dy):
-    """The three passes under the library's own plans, no bias: y, dx, dw."""
+    """The three passes under the library's own plans, no bias: y, dx, dw.  All on split operands."""
     k = shape[4]
+    assert all(D.conv_plan_split(shape, p) for p in range(3))
     return run_conv(shape, x, wt, np.zeros(k, np.float32), dy, 0, None)[:3]
 
 
@@ -705,7 +712,7 @@ def test_conv_split_operands(shape, spread):
     """Large passes multiply operands split into two half-precision terms under a power of two
     that each tile chooses from its data.  even: no call to choose twice.  growing: channels
     (filters, pixels) grow from 2^-40 to 1, so a tile's later stages exceed its first scale again
-    and again.  rows: images 2^12 apart, each compared by itself: a value 2^24 below its tile's
+    and again; the filter gradient, whose rows they are, is compared at each row's own size.  rows: images 2^12 apart, each compared by itself: a value 2^24 below its tile's
     largest still has full precision."""
     n, h, w, c, k, r, s, st, pad, pad_w = shape
     P, Q = out_hw(h, r, st, pad), out_hw(w, s, st, pad_w)
@@ -713,9 +720,11 @@ def test_conv_split_operands(shape, spread):
     x = synth.random_tensor(seed, (n, h, w, c))
     wt = synth.random_tensor(seed + 1, (k, r, s, c))
     dy = synth.random_tensor(seed + 2, (n, P, Q, k))
+    size = 1.0   # of the filter gradient's rows
     if spread == "growing":
-        x = x * np.exp2(np.linspace(-40, 0, c)).astype(np.float32)
-        dy = dy * np.exp2(np.linspace(-40, 0, k)).astype(np.float32)
+        fc, fk = np.exp2(np.linspace(-40, 0, c)), np.exp2(np.linspace(-40, 0, k))
+        x, dy = x * fc.astype(np.float32), dy * fk.astype(np.float32)
+        size = fk.reshape(k, 1, 1, 1) * fc
     elif spread == "rows":
         f = np.exp2(-12.0 * (np.arange(n) % 3)).astype(np.float32).reshape(n, 1, 1, 1)
         x, dy = x * f, dy * f
@@ -732,14 +741,29 @@ def test_conv_split_operands(shape, spread):
     else:
         assert rel_err(y, y_ref) <= tol(r * s * c)
         assert rel_err(dx, dx_ref) <= tol(r * s * k)
-    assert rel_err(dw, dw_ref) <= tol(n * P * Q)
+    assert rel_err(dw / size, dw_ref / size) <= tol(n * P * Q)
 
 
-APART_SHAPES = [s for s in SPLIT_SHAPES if s[7] == 1] + [(10, 30, 30, 96, 144, 3, 3, 2, 1, 1),
-                                                         (16, 28, 28, 128, 160, 1, 1, 1, 0, 0)]
+@pytest.mark.parametrize("shape", SPLIT_SHAPES, ids=[str(s) for s in SPLIT_SHAPES])
+def test_conv_split_dropped_term(shape):
+    """Every operand 1 + 2^-11, halfway between two half-precision numbers: the remainders are as large as
+    they get and all of one sign, and the product of the two low terms, which is left out, is 2^-22 of each
+    product.  Sums round once per 8 products, by at most 2^-24 of what they have reached, and once more per
+    split-K slot (at most 10 roundings in order)."""
+    n, h, w, c, k, r, s, st, pad, pad_w = shape
+    P, Q = out_hw(h, r, st, pad), out_hw(w, s, st, pad_w)
+    one = np.float32(1 + 2.0 ** -11)
+    x, wt, dy = (np.full(d, one, np.float32) for d in ((n, h, w, c), (k, r, s, c), (n, P, Q, k)))
+    y, dx, dw = _passes(shape, x, wt, dy)
+    refs = [OC.conv2d_forward(x, wt, np.zeros(k, np.float32), st, (pad, pad_w)),
+            OC.conv2d_backward_data(dy, wt, (h, w), st, (pad, pad_w)),
+            OC.conv2d_backward_filter(x, dy, (r, s), st, (pad, pad_w))]
+    for name, a, ref, terms in zip(("y", "dx", "dw"), (y, dx, dw), refs, (r * s * c, r * s * k, n * P * Q)):
+        bar = 2.0 ** -22 + (terms / 8 + 10) * 2.0 ** -24
+        assert (np.abs(a - ref) <= bar * ref).all(), (name, np.abs(a - ref).max() / ref.max(), bar)
 
 
-@pytest.mark.parametrize("shape", APART_SHAPES, ids=str)
+@pytest.mark.parametrize("shape", SPLIT_SHAPES + [(16, 28, 28, 128, 160, 1, 1, 1, 0, 0)], ids=str)
 @pytest.mark.parametrize("side", ["rows", "columns"])
 def test_conv_split_rows_apart(shape, side):
     """A row's result does not depend on how large its neighbours are.  Every other row of one operand (an
@@ -754,7 +778,6 @@ def test_conv_split_rows_apart(shape, side):
     refs = [OC.conv2d_forward(x, wt, np.zeros(k, np.float32), st, (pad, pad_w)),
             OC.conv2d_backward_data(dy, wt, (h, w), st, (pad, pad_w)),
             OC.conv2d_backward_filter(x, dy, (r, s), st, (pad, pad_w))]
-    assert all(D.conv_plan_split(shape, p) for p in range(3))
     for gap in (24, 28, 40, 60):
         def alt(*dims):   # 1, 2^-gap, 1, ...
             return np.where(np.arange(np.prod(dims)) % 2, 2.0 ** -gap, 1.0).astype(np.float32).reshape(dims)
@@ -777,7 +800,6 @@ def test_conv_split_one_huge_value():
     """One value of 1e30 in x and in dy: the outputs that it does not reach are what they are without it."""
     shape = (4, 23, 21, 112, 152, 3, 3, 1, 1, 1)
     n, h, w, c, k, r, s, st, pad, pad_w = shape
-    assert all(D.conv_plan_split(shape, p) for p in range(3))
     x, wt = synth.random_tensor(21, (n, h, w, c)), synth.random_tensor(22, (k, r, s, c))
     dy = synth.random_tensor(23, (n, h, w, k))
     ref = _passes(shape, x, wt, dy)
@@ -794,30 +816,46 @@ def test_conv_split_one_huge_value():
     assert rel_err(dw * far, ref[2] * far) <= tol(n * h * w)
 
 
-def test_conv_split_operands_nonfinite():
-    """Infinities and NaNs come out where float32 products put them: an infinite input gives
-    infinities (or NaNs where it meets a zero weight) in its own windows only, and a value that
-    half precision would round past its largest stays finite."""
-    shape = (4, 20, 20, 64, 64, 3, 3, 1, 1, 1)
+@pytest.mark.parametrize("chan", [64, 68], ids=["lean", "general"])
+def test_conv_split_operands_nonfinite(chan):
+    """Infinities and NaNs come out where float32 products put them: an infinite value gives
+    infinities (or NaNs where it meets a zero) in the results that it reaches only, and 1e38, far past
+    what half precision holds, stays finite and leaves its tile's other results alone.  The other values are integers, whose
+    sums are exact.  (dy's lie inside the image: float32 products make a NaN of an infinite dy and
+    the padding.)"""
+    shape = (18, 20, 20, chan, chan, 3, 3, 1, 1, 1)
     n, h, w, c, k, r, s, st, pad, pad_w = shape
     rng = np.random.default_rng(5)
     x = rng.integers(-3, 4, (n, h, w, c)).astype(np.float32)
     wt = rng.integers(-2, 3, (k, r, s, c)).astype(np.float32)
     dy = rng.integers(-3, 4, (n, h, w, k)).astype(np.float32)
     x[1, 5, 7, 3], x[2, 9, 0, 10], x[3, 19, 19, 63] = np.inf, -np.inf, np.nan
-    x[0, 3, 3, 5] = 3.0e38
+    x[0, 3, 3, 5] = 1.0e38
     wt[:, 1, 1, 5] = 1.0
-    y, _dx, _dw = _passes(shape, x, wt, dy)
-    t = __import__("torch")
-    ref = t.nn.functional.conv2d(t.from_numpy(x).permute(0, 3, 1, 2).double(),
-                                 t.from_numpy(wt).permute(0, 3, 1, 2).double(), padding=1).permute(0, 2, 3, 1).numpy()
-    with np.errstate(over="ignore"):
-        ref = ref.astype(np.float32)
-    assert np.array_equal(np.isnan(y), np.isnan(ref))
-    assert np.array_equal(np.isposinf(y), np.isposinf(ref)) and np.array_equal(np.isneginf(y), np.isneginf(ref))
-    fine = np.isfinite(ref)
-    assert fine.mean() > 0.9
-    assert np.all(np.abs(y[fine] - ref[fine]) <= 1e-6 * np.maximum(np.abs(ref[fine]), 1.0) + 1e-5 * 64 * 9)
+    dy[4, 9, 9, 7], dy[5, 2, 17, 20], dy[6, 11, 3, 33] = np.inf, -np.inf, np.nan
+    dy[7, 8, 8, 9] = 1.0e38
+    x[7, 7:10, 7:10, 5] = 0   # no filter gradient sums both large values: no sum overflows
+    wt[9, 1, 1, :] = 1.0
+    y, dx, dw = _passes(shape, x, wt, dy)
+    x64, w64, dy64 = x.astype(np.float64), wt.astype(np.float64), dy.astype(np.float64)
+    pad4 = ((0, 0), (1, 1), (1, 1), (0, 0))
+    xp, dyp = np.pad(x64, pad4), np.pad(dy64, pad4)
+    refs = [np.zeros(y.shape), np.zeros(dx.shape), np.zeros(dw.shape)]
+    with np.errstate(over="ignore", invalid="ignore"):
+        for i in range(3):
+            for j in range(3):
+                win = xp[:, i:i + h, j:j + w]
+                refs[0] += win @ w64[:, i, j, :].T
+                refs[1] += dyp[:, 2 - i:2 - i + h, 2 - j:2 - j + w] @ w64[:, i, j, :]
+                refs[2][:, i, j, :] = dy64.reshape(-1, k).T @ win.reshape(-1, c)
+        refs = [a.astype(np.float32) for a in refs]
+    for name, got, ref, least in zip(("y", "dx", "dw"), (y, dx, dw), refs, (0.9, 0.9, 0.8)):
+        assert np.array_equal(np.isnan(got), np.isnan(ref)), name
+        assert np.array_equal(np.isposinf(got), np.isposinf(ref)), name
+        assert np.array_equal(np.isneginf(got), np.isneginf(ref)), name
+        fine = np.isfinite(ref)
+        assert fine.mean() > least, name
+        assert np.all(np.abs(got[fine] - ref[fine]) <= 1e-6 * np.maximum(np.abs(ref[fine]), 1.0)), name
 
 
 @pytest.mark.parametrize("cfg", [(2, 11, 10, 8, 3, 3, 1), (1, 9, 9, 4, 4, 4, 1), (3, 10, 13, 12, 3, 4, 0),
