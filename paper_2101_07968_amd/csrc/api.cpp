@@ -224,7 +224,6 @@ extern "C" int dc_conv2d_forward(const dc_conv_shape *sh, const float *x, const 
 // device current) at the first call there, and only that address is handed
 // to kernels.
 namespace {
-constexpr size_t NOALLOC_SCRATCH_BYTES = size_t(64) << 20;
 constexpr int NOALLOC_MAX_DEVICES = 64;
 static __device__ __align__(256) unsigned char noalloc_scratch[NOALLOC_SCRATCH_BYTES];
 std::mutex g_noalloc_mu;

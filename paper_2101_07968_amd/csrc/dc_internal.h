@@ -93,6 +93,10 @@ struct GemmPlan {
     bool direct;
 };
 
+// Scratch of dc_conv2d_forward_noalloc.  The cost model keeps forward plans of
+// split operands within it.
+constexpr size_t NOALLOC_SCRATCH_BYTES = size_t(64) << 20;
+
 enum PlanSource { PLAN_MODEL = 0, PLAN_TABLE = 1, PLAN_PINNED = 2, PLAN_FC = 3, PLAN_DIRECT = 4 };
 
 bool conv_geom_from_shape(const dc_conv_shape &sh, ConvGeom *g);

@@ -143,3 +143,38 @@ def test_plan_split_names_the_form():
     assert not D.conv_plan_split((32, 224, 224, 3, 64, 3, 3, 1, 1, 1), 0)
     with pytest.raises(D.DcError):
         D.conv_plan_split(big, 3)
+
+
+def test_forward_plans_fit_the_static_scratch():
+    """The entry without a workspace argument takes every forward shape whose padded copies (c % 4 != 0) alone
+    fit its 64 MiB: the model's split-K factor leaves room for them, and the table's plans fit too."""
+    import random
+    rng = random.Random(4)
+
+    def r256(b):
+        return (b + 255) // 256 * 256
+
+    shapes = [(59, 15, 15, 181, 1616, 5, 5, 2, 2, 2), (8, 132, 132, 26, 48, 11, 11, 1, 5, 5)]
+    while len(shapes) < 4000:
+        r = rng.choice([1, 3, 3, 5, 7, 11])
+        st = rng.choice([1, 1, 2])
+        hw = int(2 ** rng.uniform(2, 8))
+        if hw >= r:
+            shapes.append((rng.randint(1, 128), hw, hw, int(2 ** rng.uniform(2, 10)), int(2 ** rng.uniform(3, 11)),
+                           r, r, st, r // 2, r // 2))
+    shapes += [g for pas, g, _ in _table() if pas == 0]
+    split = 0
+    for g in shapes:
+        n, h, w, c, k, r, s, *_ = g
+        if n * h * w * max(c, k) >= 2 ** 31:   # refused as a shape
+            continue
+        _mt, _nt, sp, m, ng, _kg, _ph, src = D.conv_plan_info(g, 0)
+        if src > 1:
+            continue
+        cp = (c + 3) // 4 * 4
+        pads = (r256(4 * n * h * w * cp) + r256(4 * k * r * s * cp)) if c % 4 else 0
+        sums = r256(4 * sp * m * ng) if sp > 1 else 0
+        if D.conv_plan_split(g, 0) and pads <= 64 << 20:
+            assert sums + pads <= 64 << 20, (g, sp)
+            split += c % 4 != 0 and sp > 1
+    assert split > 20
