@@ -73,8 +73,8 @@ struct GemmPlan {
     int splits;           // split-K factor (1 = no split)
     int kt_per_split;     // K stages (of depth kt) per split
     bool av, bv;          // float4 operand loads possible
-    bool tu;              // lean address mode: FWD C % 16 == 0; DGRAD K % 16 == 0, C % 4 == 0 (both R S <= 32);
-                          // WGRAD K, C % 4 == 0
+    bool tu;              // lean address mode: FWD C % 16 == 0; DGRAD K % 16 == 0, C % 4 == 0; WGRAD K, C % 4 == 0
+    int taps;             // FWD, DGRAD: most filter taps of a (phase's) reduction
     bool split;           // operands split into half-precision terms (float4 operands, 5e8 flops, Kg >= 96)
     int cpad;             // FWD / WGRAD with C % 4 != 0: padded channel count, else 0
     size_t pad_x_off;     // workspace offsets of the padded x and of the padded w (FWD) or dw (WGRAD)

@@ -101,6 +101,9 @@ SMALL = [
     (2, 19, 18, 16, 24, 3, 5, 2, 1, 2),
     (2, 15, 15, 16, 24, 3, 3, 2, 0, 0),
     (3, 21, 20, 16, 32, 1, 3, 1, 0, 1),
+    # lean stages with more filter taps than a word has bits
+    (2, 12, 13, 16, 32, 7, 7, 1, 3, 3),
+    (2, 19, 17, 32, 16, 7, 9, 2, 3, 4),
 ]
 
 
@@ -696,6 +699,12 @@ SPLIT_SHAPES = [
     (10, 30, 30, 96, 144, 3, 3, 2, 1, 1),
     # images of fewer pixels than a stage (the filter gradient steps whole images)
     (160, 3, 3, 208, 160, 3, 3, 1, 1, 1),
+    # lean stages of 32 filter taps (one word of bits), 33 and 49 (tested per stage), and a strided
+    # filter of 49 whose data gradient's phases hold 16 at most
+    (6, 18, 17, 64, 64, 4, 8, 1, 2, 4),
+    (7, 18, 17, 64, 64, 3, 11, 1, 1, 5),
+    (5, 18, 17, 64, 64, 7, 7, 1, 3, 3),
+    (12, 29, 29, 48, 64, 7, 7, 2, 3, 3),
 ]
 
 
