@@ -689,6 +689,22 @@ def test_add_relu_backward(n):
     np.testing.assert_array_equal(host(d0), (acc + m).astype(np.float32))
 
 
+def test_conv_filter_gradient_large_images():
+    """Images of 288 MB that give one output pixel each: the 16 pixels of a stage would reach past 2^32 bytes.
+    Only the window has a part in the filter gradient; every value outside it is infinite."""
+    shape = (1, 4240, 4241, 4, 8, 3, 3, 5000, 0, 0)
+    t = __import__("torch")
+    x = t.full(shape[:4], math.inf, dtype=t.float32, device="cuda")
+    win, dy = synth.random_tensor(31, (3, 3, 4)), synth.random_tensor(32, (1, 1, 1, 8))
+    x[0, :3, :3] = dev(win)
+    dyd, dw = dev(dy), zeros((8, 3, 3, 4))
+    sh = conv_shape(*shape)
+    ws_t, ws, wsb = scratch(D.lib().dc_conv2d_workspace_bytes(ctypes.byref(sh)))
+    D.call("dc_conv2d_backward_filter", ctypes.byref(sh), x.data_ptr(), dyd.data_ptr(), dw.data_ptr(), None, ws, wsb,
+           stream())
+    np.testing.assert_array_equal(host(dw), dy.reshape(8, 1, 1, 1) * win)
+
+
 # ---------------------------------------------------------------- split operands
 
 SPLIT_SHAPES = [
