@@ -20,6 +20,7 @@ from oracle import cnn as OC
 from oracle import nets as ON
 from paper_2101_07968_amd import _lib as D
 from tests.gpu_helpers import dev, host, rel_err, scratch, stream, zeros
+from tests.test_plan_table import PRECISE
 
 pytestmark = pytest.mark.gpu
 
@@ -687,6 +688,22 @@ def test_add_relu_backward(n):
     d0 = dev(acc)
     D.call("dc_add_relu_backward", dyd.data_ptr(), yd.data_ptr(), 1, d0.data_ptr(), 0, None, n, stream())
     np.testing.assert_array_equal(host(d0), (acc + m).astype(np.float32))
+
+
+@pytest.mark.parametrize("case", PRECISE, ids=str)
+def test_conv_precise_plans(case):
+    """Passes whose plan is kept for its precision: no further from 64 bits than the float32 form was under its
+    own plan (1% for the two seeds' scatter)."""
+    from perf import cases
+    pas, shape = case
+    conv = cases.conv("precise", *shape)
+    errs = []
+    for seed in (1, 2):
+        st = cases.prepare(conv, seed)
+        name = ("y", "dx", "dw")[pas]
+        got, ref = cases.run(st)[name].double(), cases.exact(conv, seed)[name]
+        errs.append(float((got - ref).norm() / ref.norm()))
+    assert sum(errs) / 2 <= 1.01 * PRECISE[case], errs
 
 
 def test_conv_filter_gradient_large_images():

@@ -177,3 +177,29 @@ def test_forward_plans_fit_the_static_scratch():
             assert sums + pads <= 64 << 20, (g, sp)
             split += c % 4 != 0 and sp > 1
     assert split > 20
+
+
+# (pass, shape): relative 2-norm error against 64 bits of the float32 form under the plan that it had, on the
+# inputs of perf/cases.py (mean of two seeds)
+PRECISE = {
+    (1, (4, 16, 16, 8, 16, 3, 3, 1, 1, 1)): 1.514e-7,
+    (0, (32, 14, 14, 16, 48, 5, 5, 1, 2, 2)): 1.736e-7,
+    (0, (32, 7, 7, 48, 128, 5, 5, 1, 2, 2)): 1.546e-7,
+    (0, (32, 17, 17, 192, 224, 1, 7, 1, 0, 3)): 2.285e-7,
+    (0, (32, 14, 14, 512, 512, 3, 3, 1, 1, 1)): 2.959e-7,
+    (2, (64, 14, 14, 512, 512, 3, 3, 2, 1, 1)): 2.455e-7,
+    (2, (32, 14, 14, 128, 256, 3, 3, 1, 1, 1)): 1.500e-7,
+    (2, (32, 14, 14, 528, 256, 1, 1, 1, 0, 0)): 1.547e-7,
+    (2, (32, 35, 35, 192, 224, 3, 3, 1, 1, 1)): 3.185e-7,
+    (2, (32, 71, 71, 192, 192, 3, 3, 2, 0, 0)): 3.305e-7,
+    (2, (32, 224, 224, 64, 64, 3, 3, 1, 1, 1)): 5.169e-7,
+}
+
+
+def test_precise_plans_are_picked():
+    """Plans kept for their precision come before the table of the fastest ones and are not listed there."""
+    listed = {(pas, g) for pas, g, _ in _table()}
+    for pas, g in PRECISE:
+        assert (pas, g) not in listed
+        info = D.conv_plan_info(g, pas)
+        assert info[7] == 1 and info[2] > 1 and info[:3] in D.conv_plan_candidates(g, pas), (pas, g, info)
