@@ -31,6 +31,8 @@ import numpy as np
 import pytest
 
 from oracle import cnn as OC
+from paper_2101_07968_amd import _lib as D
+from paper_2101_07968_amd import nets as PN
 from tests import layerwise
 from tests.gpu_helpers import rel_err, report, update_err
 from tests.test_gpu_step import UNPACED, gpu_decisions, plans_for, setup_model
@@ -152,3 +154,34 @@ def test_full_batch_matches_oracle(name, batch, seed):
         worst_ops = layerwise.check_ops(name, onet, y, params, res)
         report(f"layer-wise {name} b{batch}: worst error / bar per op kind: "
                + ", ".join(f"{k} {v:.3f}" for k, v in sorted(worst_ops.items())))
+
+
+def test_googlenet_batch_gradients_with_gpu_decisions():
+    """GoogLeNet at its own batch, where most of its passes multiply split operands: its gradients move by about
+    1e-4 to 1e-3 with any change of rounding, because some of its 1.5e8 ReLU and max-pool decisions lie within
+    rounding of a tie.  With the GPU's own decisions given to the oracle every tensor stays within the bar of a
+    single pass of 1000 terms (2e-5), so nothing but those decisions differs."""
+    name, batch, seed = "googlenet", 32, 5
+    ops, hwc, _ = PN.build(name)
+    split = [D.conv_plan_split(g, p) for _i, g, first in PN.conv_geoms(ops, hwc, batch) for p in range(3)
+             if not (first and p == 1)]
+    assert sum(split) > len(split) // 2, split
+    model, onet, xd, yd, x, y, params = setup_model(name, batch, seed)
+    print(f"full batch {name}: dc_step", flush=True)
+    st = model.step(xd, yd, plans_for(model.L, seed=seed)["random"], UNPACED)
+    _p, g = model.ps_read()
+    dec = gpu_decisions(model, onet, name)
+    model.close()
+    print(f"full batch {name}: oracle iteration, with its own and with the GPU's decisions", flush=True)
+    own = onet.loss_and_grads(x, y, params, keep=True)
+    flips = sum(int((dec[i] != own[3][i]).sum()) for i in dec)
+    loss_d, g_d = onet.loss_and_grads(x, y, params, decisions=dec)
+    errs = {(i, pname): rel_err(g[off:off + int(np.prod(shape))], g_d[off:off + int(np.prod(shape))])
+            for i, slots in enumerate(onet.pslots) for pname, (off, shape) in slots.items()}
+    worst = max(errs, key=errs.get)
+    plain = np.linalg.norm(g - own[1]) / np.linalg.norm(own[1])
+    report(f"full batch {name} b{batch}: {sum(split)} of {len(split)} passes on split operands; {flips} decisions of "
+           f"{sum(d.size for d in dec.values())} differ from the oracle's own, gradients {plain:.1e} from it; with the "
+           f"GPU's decisions worst tensor {errs[worst]:.1e} at {worst}")
+    assert abs(st["loss"] - loss_d) <= 1e-6 * abs(loss_d)
+    assert errs[worst] <= 2e-5, (worst, errs[worst])
