@@ -42,11 +42,14 @@ int elapsed_ns(hipEvent_t a, hipEvent_t b, int64_t *out) {
     return DC_OK;
 }
 
-// Poll an event until it completes or the deadline passes: for the first 200 us
-// without a pause (a sleep of 20 us returns after 70-80, a fifth of a small
-// network's whole iteration, once per push segment), then every 20 us or so.
-int wait_event(hipEvent_t e, Clock::time_point deadline) {
-    const Clock::time_point nap_from = Clock::now() + std::chrono::microseconds(200);
+// Poll an event until it completes or the deadline passes.  From 100 us before
+// `due`, the earliest time at which it can complete (or from now, if that is past),
+// polls follow each other without a pause for 300 us: a sleep of 20 us returns
+// after 70-80, a fifth of a small network's whole iteration, once per push segment.
+// Before and after, every 20 us or so.
+int wait_event(hipEvent_t e, Clock::time_point due, Clock::time_point deadline) {
+    const Clock::time_point spin_from = std::max(due - std::chrono::microseconds(100), Clock::now());
+    const Clock::time_point nap_from = spin_from + std::chrono::microseconds(300);
     for (;;) {
         hipError_t r = hipEventQuery(e);
         if (r == hipSuccess)
@@ -56,7 +59,7 @@ int wait_event(hipEvent_t e, Clock::time_point deadline) {
         const Clock::time_point now = Clock::now();
         if (now > deadline)
             return fail(DC_ETIMEOUT, "watchdog expired while waiting for the GPU");
-        if (now >= nap_from)
+        if (now < spin_from || now >= nap_from)
             std::this_thread::sleep_for(std::chrono::microseconds(20));
     }
 }
@@ -91,6 +94,12 @@ std::vector<Seg> push_segs(const dc_plan_t *plan, int L) {
 }
 
 uint64_t to_ticks(double ns, double hz) { return (uint64_t)std::ceil(ns * hz * 1e-9); }
+
+// The least time that one takes: overhead and, on a paced link, the bytes' share.
+std::chrono::nanoseconds link_time(const dc_link *link, size_t bytes) {
+    const double ns = (double)link->dt_emul_ns + (link->paced ? (double)bytes / link->bytes_per_s * 1e9 : 0.0);
+    return std::chrono::nanoseconds((int64_t)std::min(ns, 1e15));
+}
 
 // One transmission mini-procedure of `bytes` on stream s.
 int transmit(dc_model *m, void *dst, const void *src, size_t bytes, hipMemcpyKind kind, const dc_link *link,
@@ -189,9 +198,11 @@ int step_impl(dc_model *m, const dc_batch *b, dc_plan_t *plan, const dc_profile_
 
     // pull stream
     DC_HIP(hipEventRecord(m->ev_t0, m->pull_s));
+    Clock::time_point due = t_host0; // no push is complete before: here, all pulls
     for (size_t j = 0; j < pulls.size(); ++j) {
         size_t off;
         size_t bytes = seg_bytes(m, pulls[j], &off);
+        due += link_time(link, bytes);
         DC_TRY(transmit(m, m->dparams() + off, m->ps_params + off, bytes, hipMemcpyHostToDevice, link,
                         m->slots() + j, m->ev_pull_start[j], m->ev_pull_done[j], m->pull_s));
     }
@@ -254,11 +265,12 @@ int step_impl(dc_model *m, const dc_batch *b, dc_plan_t *plan, const dc_profile_
             if (hipEventQuery(m->ev_push_done[i]) == hipErrorNotReady)
                 hidden |= 2;
         }
-        DC_TRY(wait_event(m->ev_push_done[i], deadline));
-        if (i + 1 == pushes.size())
-            t_last_push = Clock::now();
         size_t off;
         size_t bytes = seg_bytes(m, pushes[i], &off);
+        DC_TRY(wait_event(m->ev_push_done[i], due + link_time(link, bytes), deadline));
+        due = Clock::now(); // pushes follow one another
+        if (i + 1 == pushes.size())
+            t_last_push = due;
         sgd_range(m, off, bytes / sizeof(float));
     }
     const int64_t sgd_tail = ns_since(t_last_push);
