@@ -364,7 +364,8 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f32",
+        # float32 tensors and sums; large passes multiply each operand as two half-precision terms
+        "dtype": "f32 (products of two f16 terms per operand, f32 sums)",
         "data": "synthetic (seeded N(0,1) images, uniform labels, He-normal weights)",
         "config": {"workload": name, "global_batch": batch, "image": list(hwc), "classes": classes,
                    "link": f"{args.link_gbps} Gb/s paced" if paced else "unpaced host interface",

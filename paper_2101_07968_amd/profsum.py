@@ -13,10 +13,11 @@ traffic: FETCH_SIZE / WRITE_SIZE (KiB per dispatch) of the igemm dispatches of a
 `bench.py --kernels-only` run, scaled by what the same counters read for the
 256 MiB calibration copy, against the algorithmic bytes of those launches.
 
-mfma: SQ_INSTS_VALU_MFMA_MOPS_F32 and _F16 (units of 512 flops; a split pass issues
-three half-precision products per float32 one), SQ_VALU_MFMA_BUSY_CYCLES and GRBM_GUI_ACTIVE of the same igemm dispatches, with their durations from a
-kernel-trace run: MFMA flops issued against algorithmic flops, and the fraction
-of SIMD cycles the matrix cores were busy.
+mfma: SQ_INSTS_VALU_MFMA_MOPS_F32 and _F16 (units of 512 flops; a split pass
+issues three half-precision products per float32 one), SQ_VALU_MFMA_BUSY_CYCLES
+and GRBM_GUI_ACTIVE of the same igemm dispatches, with their durations from a
+kernel-trace run: MFMA flops issued against algorithmic flops, the clock, and the
+fraction of SIMD cycles the matrix cores were busy.
 
 hbm: FETCH_SIZE / WRITE_SIZE of every dispatch of a run that includes a
 calibration copy (the non-GEMM report does), over durations from a
