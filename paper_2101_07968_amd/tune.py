@@ -10,7 +10,8 @@ interleaved rounds; the median decides.  A shape enters the table only when
 its winner beats the cost model's choice by more than --margin, so timing
 noise does not churn plans.  A pass that runs on the weight-streaming FC
 data-gradient kernel (plan source 3) or on the direct RGB-layer kernels (source 4) is
-skipped.  Needs a GPU; run from the repository root:
+skipped, and so are the passes whose plan is kept for its precision (kPrecise in
+plan_table.cpp).  Needs a GPU; run from the repository root:
 
     python -m paper_2101_07968_amd.tune --out plan_table.inc
 
@@ -21,11 +22,21 @@ from __future__ import annotations
 
 import argparse
 import ctypes
+import os
+import re
 import statistics
 import sys
 import time
 
 PASS_NAMES = ("fwd", "dgrad", "wgrad")
+
+
+def precise_passes():
+    """(pass, geometry) of every plan of plan_table.cpp that is kept for its precision."""
+    path = os.path.join(os.path.dirname(os.path.abspath(__file__)), "csrc", "plan_table.cpp")
+    block = re.search(r"kPrecise\[\] = \{(.*?)\n\};", open(path).read(), re.S).group(1)
+    rows = [[int(v) for v in m.split(",")] for m in re.findall(r"\{([-\d,\s]+)\}", block)]
+    return {(r[0], tuple(r[1:11])) for r in rows}
 
 
 def _geometries(PN, workloads):
@@ -54,6 +65,7 @@ def main(argv=None):
 
     names = [w for w in a.workloads.split(",") if w] or sorted(PN.WORKLOADS)
     geoms = _geometries(PN, names)
+    precise = precise_passes()
     s = torch.cuda.current_stream()
     sp = s.cuda_stream
     print(f"[tune] {len(geoms)} geometries of {','.join(names)} on "
@@ -74,6 +86,9 @@ def main(argv=None):
         line = []
         for pas in (0, 1, 2):
             if pas == 1 and rec["first"]:
+                continue
+            if (pas, g) in precise:
+                line.append(f"{PASS_NAMES[pas]} plan kept for its precision")
                 continue
             src = D.conv_plan_info(g, pas)[7]
             if src in (3, 4):   # the FC streaming kernel, the RGB layer's direct kernels
